@@ -46,6 +46,58 @@ def check_m0_writes(asm_text):
     return bad
 
 
+def _scalars(operand):
+    m = re.fullmatch(r"s\[(\d+):(\d+)\]", operand) or re.fullmatch(r"s(\d+)()", operand)
+    return set(range(int(m[1]), int(m[2] or m[1]) + 1)) if m else set()
+
+
+def check_request_scalars(asm_text):
+    """A scalar register that a vector instruction writes may be read by a memory instruction five
+    wait states later at the earliest.  The compiler keeps that distance for its own instructions
+    but does not see the direct-to-LDS requests inside their asm statements: a descriptor that it
+    computed in vector registers and moved over right in front of a request would be read stale,
+    and the request would go to a wild address.  Returns the requests that are too near, along
+    every path of up to five instructions."""
+    STATES = 5
+    bad, pending = set(), {}         # label -> writes still in flight where something jumps to it
+    for _ in range(2):               # a second pass has the backward jumps too
+        live = {}                    # scalar register -> wait states since a vector instruction wrote it
+        fell = True
+        for number, line in enumerate(asm_text.splitlines(), 1):
+            text = line.split(";")[0].strip()
+            label = re.fullmatch(r"([.\w$]+):", text)
+            if label:
+                if not fell:
+                    live = {}
+                for reg, age in pending.get(label[1], {}).items():
+                    live[reg] = min(age, live.get(reg, age))
+                fell = True
+                continue
+            if not text or text.startswith("."):
+                continue
+            op, _, rest = text.partition(" ")
+            operands = re.findall(r"[^\s,\[]+(?:\[[^\]]*\])?", rest)
+            if op.startswith("buffer_load") and operands and operands[-1] == "lds":
+                used = set().union(*(_scalars(o) for o in operands))
+                if any(live.get(reg, STATES) < STATES for reg in used):
+                    bad.add(f"line {number}: {text}")
+            step = int(operands[0], 0) + 1 if op == "s_nop" else 1
+            live = {reg: age + step for reg, age in live.items() if age + step < STATES}
+            if op.startswith("v_") and operands:
+                # (the carry or scale result of a few instructions is their second operand)
+                results = operands[:2] if re.search(r"_co_|_co_u32|v_mad_[ui]64|v_div_scale", op) else operands[:1]
+                live.update({reg: 0 for o in results for reg in _scalars(o)})
+            elif op.startswith("s_") and operands:
+                for reg in _scalars(operands[0]):
+                    live.pop(reg, None)
+            if op.startswith("s_branch") or op.startswith("s_cbranch"):
+                into = pending.setdefault(operands[0], {})
+                for reg, age in live.items():
+                    into[reg] = min(age, into.get(reg, age))
+            fell = op not in ("s_branch", "s_endpgm", "s_setpc_b64")
+    return sorted(bad)
+
+
 def _compile(src, tmp, extra):
     """One source to an object; the device assembly is kept beside it and checked."""
     stem = os.path.splitext(os.path.basename(src))[0]
@@ -58,7 +110,12 @@ def _compile(src, tmp, extra):
     if not found:
         raise RuntimeError(f"no device assembly of {src} was kept: cannot check M0 writes")
     for path in found:
-        bad = check_m0_writes(open(path).read())
+        asm_text = open(path).read()
+        bad = check_request_scalars(asm_text)
+        if bad:
+            raise RuntimeError(f"requests too near behind a vector write of their scalar registers in the device code of {src}: "
+                               + "; ".join(bad[:5]))
+        bad = check_m0_writes(asm_text)
         if bad:
             raise RuntimeError(f"compiler-generated writes to M0 in the device code of {src} "
                                "(they would redirect the direct-to-LDS requests): " + "; ".join(bad[:5]))

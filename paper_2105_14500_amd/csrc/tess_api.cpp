@@ -127,17 +127,8 @@ static tess_status make_plan(const GemmArgs& g, Plan& p)
     if (g.lda % 8 != 0 || g.ldb % 8 != 0) return TESS_ERR_ALIGN;
     for (int t = 0; t < g.q; ++t)
         if (!aligned16(g.a[t]) || !aligned16(g.b[t])) return TESS_ERR_ALIGN;
-    // 32-bit byte offsets inside a panel (the loaders add up to 4 KiB to every offset)
     const int64_t a_rows = g.a_kc ? g.M : g.Kp, b_rows = g.b_kc ? g.N : g.Kp;
-    const int64_t lim = ((int64_t)1 << 32) - 4096;
-    if (a_rows * g.lda * 2 >= lim || b_rows * g.ldb * 2 >= lim) return TESS_ERR_UNSUPPORTED;
-    // panels with a ragged last stage: the loader tells what lies past their end by bit 31 of the
-    // offset, so larger ones go to the kernel that takes any shape
-    if (!p.direct && (a_rows * g.lda * 2 >= lim / 2 || b_rows * g.ldb * 2 >= lim / 2)) {
-        p.path = Path::Generic;
-        p.splits = 1;
-        p.ws_bytes = 0;
-    }
+    if (a_rows * g.lda * 2 >= DMA_PANEL_LIMIT || b_rows * g.ldb * 2 >= DMA_PANEL_LIMIT) return TESS_ERR_UNSUPPORTED;
     return TESS_OK;
 }
 

@@ -11,6 +11,9 @@
 namespace tess {
 
 constexpr int BK_HOST = 64;   // K extent of one LDS stage of the MFMA path
+// Bytes of a panel (rows x leading dimension) from which the MFMA path refuses it: the loaders address
+// it with 32-bit byte offsets, to which they add up to 4 KiB.
+constexpr int64_t DMA_PANEL_LIMIT = ((int64_t)1 << 32) - 4096;
 
 // One launch computes  OUT[M,N] = epilogue( sum_{t<q} Aop_t * Bop_t ), where the
 // contraction length per panel is Kp and the operands of step t are the t-th

@@ -38,13 +38,13 @@ namespace tess {
 // Tiles are always written linearly (granule index = it*256 + thread), so the
 // swizzle is applied on the global-memory side of the copy.
 template <int BK>
-__device__ __forceinline__ int swz_kc(int r)
+__host__ __device__ __forceinline__ int swz_kc(int r)
 {
     constexpr int CH = BK / 8, RPL = 128 / BK;   // chunks per row, rows per 256-byte bank line
     return (r / RPL) % CH;
 }
 template <int R>
-__device__ __forceinline__ int swz_mc(int kr)
+__host__ __device__ __forceinline__ int swz_mc(int kr)
 {
     // R = 64: a k-row is half a bank line, so k-rows two apart swap its halves
     // R = 32: four k-rows are one bank line already
@@ -66,27 +66,30 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// Granule index -> byte offset of that granule inside a panel at k0 = 0 and the k index
-// inside the stage at which it starts.
-template <int R, int BK, bool KC>
-__device__ __forceinline__ uint32_t granule_offset(int G, int origin, int extent, int64_t ld,
-                                                   int& kpos)
+// Granule index -> byte offset of that granule in a stage of the operand's tile at k0 = 0, from
+// the panel's first element (RELATIVE: from the tile's first one), and the k index inside the
+// stage at which it starts.  Offsets of granules that a ragged stage does not have may not fit
+// into 32 bits; they are not used (see DmaLoader).
+template <int R, int BK, bool KC, bool RELATIVE>
+__host__ __device__ __forceinline__ uint32_t granule_offset(int G, int origin, int extent, int64_t ld,
+                                                            int& kpos)
 {
     constexpr int CH = BK / 8, RG = R / 8;
+    const int from = RELATIVE ? origin : 0;
     if (KC) {
         const int r = G / CH, pc = G % CH;
         const int c = pc ^ swz_kc<BK>(r);
         int row = origin + r;
         row = row < extent ? row : extent - 1;          // rows past the edge repeat the last row
         kpos = 8 * c;
-        return (uint32_t)(((int64_t)row * ld + 8 * c) * 2);
+        return (uint32_t)(((int64_t)(row - from) * ld + 8 * c) * 2);
     } else {
         const int kr = G / RG, pg = G % RG;
         const int gidx = pg ^ swz_mc<R>(kr);
         int col = origin + 8 * gidx;
         col = col + 8 <= extent ? col : extent - 8;     // granules past the edge repeat the last one
         kpos = kr;
-        return (uint32_t)(((int64_t)kr * ld + col) * 2);
+        return (uint32_t)(((int64_t)kr * ld + (col - from)) * 2);
     }
 }
 
@@ -99,20 +102,53 @@ __device__ __forceinline__ uint32_t granule_offset(int G, int origin, int extent
 // purpose: a wavefront can start only one such request per ~100 clocks, and the
 // scalar-base form with few M0 updates is the cheapest to issue; the compiler also
 // does not track these loads, so completion is enforced by the explicit vmcnt waits
-// in front of the workgroup barriers and no blanket wait precedes LDS reads.
+// in front of the workgroup barriers and no blanket wait precedes LDS reads.  Nor does it
+// keep the five wait states between a vector instruction that writes a scalar register and a
+// request that reads it (it sees no memory instruction here): the descriptors have to come from
+// scalar arithmetic, and the build fails where one does not (paper_2105_14500_amd/build.py).
 //
-// RAGGED (panels whose contraction is no multiple of BK): the granules of a panel's last stage
-// that lie past its end get bit 31 of their offset set, which puts them outside the descriptor's
-// 2 GiB range, and the hardware returns zeros for them.  One bit per request and lane, two vector
-// instructions per request.
+// RAGGED (panels whose contraction is no multiple of BK): the requests for granules of a panel's
+// last stage that lie past its end carry the offset PAST, which is outside the descriptor's range,
+// and the hardware returns zeros for them: two vector instructions per request.  So that every
+// granule that exists is inside the range whatever the panel's size, the descriptor starts at the
+// tile's first element of the stage (less BIAS) and the scalar offset is zero.  With panels of
+// rows * ld * 2 < 2^32 - 4096 bytes (refused above that on the host) the last byte of such a granule
+// is at most min(R, rows) - 1 rows of ld (KC), or 63 rows and R elements (MC), from there:
+//   2 ld >= 8192:  < 2^32 - 4096 - 8192 + 512, plus BIAS < PAST;   2 ld < 8192:  < 255 * 8192 + 512.
+// PAST plus an immediate does not reach 2^32: the 32-bit sum would wrap to the descriptor's start,
+// which lies BIAS bytes in front of the operand.
 template <int R, int BK, bool KC, int NT, bool RAGGED>
 struct DmaLoader {
     static constexpr int NG = R * (BK / 8);      // granules per stage
     static constexpr int ITERS = NG / NT;        // requests per wavefront per stage
     static constexpr uint32_t BIAS = 3072;       // keeps (offset - imm) non-negative
+    static constexpr uint32_t PAST = 0xfffff000u;
     uint32_t off[ITERS];
     uint32_t past_end;       // RAGGED: bit it = request `it` of a panel's last stage lies past the end
     static_assert(ITERS <= 32, "a bit per request");
+    static_assert((uint64_t)PAST + BIAS + 16 <= (uint64_t)1 << 32, "no wrap");
+    static_assert((uint64_t)DMA_PANEL_LIMIT - 8192 + 512 + BIAS <= PAST, "every granule of a panel is in range");
+    static_assert(R <= 256 && 255 * 8192 + 512 + BIAS <= PAST, "as above, short rows");
+
+    // byte offset, before the immediate, of the request for granule G of a stage
+    static __host__ __device__ __forceinline__ uint32_t offset(int it, int G, int origin, int extent, int64_t ld, int& kpos)
+    {
+        return granule_offset<R, BK, KC, RAGGED>(G, origin, extent, ld, kpos) + BIAS - (it % 4) * 1024;
+    }
+    // the offset that is sent; `past`: `past_end` in a panel's last stage, else 0
+    static __host__ __device__ __forceinline__ uint32_t sent(int it, uint32_t off, uint32_t past)
+    {
+        if (!RAGGED) return off;
+        const uint32_t mask = (uint32_t)((int32_t)(past << (31 - it)) >> 31);
+        return (mask & PAST) | (~mask & off);
+    }
+    // where the descriptor of a stage starts, less BIAS: in the panel at `panel`, the tile at row or
+    // column `origin`, `adv` bytes along K
+    static __host__ __device__ __forceinline__ uint64_t start(uint64_t panel, int origin, int64_t ld, uint32_t adv)
+    {
+        if (!RAGGED) return panel;
+        return panel + (uint64_t)(KC ? origin * ld : origin) * 2 + adv;
+    }
 
     // ktail: contracted elements of a panel's last stage
     __device__ __forceinline__ void init(int lane, int wave_u, int origin, int extent, int64_t ld, int ktail)
@@ -121,30 +157,33 @@ struct DmaLoader {
         static_for<ITERS>([&](auto it) {
             const int G = (wave_u * ITERS + it) * 64 + lane;
             int kpos;
-            off[it] = granule_offset<R, BK, KC>(G, origin, extent, ld, kpos) + BIAS - (it % 4) * 1024;
+            off[it] = offset(it, G, origin, extent, ld, kpos);
             if (RAGGED && kpos >= ktail) past_end |= 1u << it;
         });
     }
-    // buffer descriptor of a panel (kept by the caller in scalar registers)
-    static __device__ __forceinline__ u32x4 descriptor(const void* panel)
+    // buffer descriptor of a panel, RAGGED: of one stage (kept by the caller in scalar registers)
+    static __device__ __forceinline__ u32x4 descriptor(uint64_t from)
     {
-        const uint64_t base = (uint64_t)(uintptr_t)panel - BIAS;
+        const uint64_t base = from - BIAS;
         u32x4 rsrc;
         rsrc[0] = __builtin_amdgcn_readfirstlane((uint32_t)base);
         rsrc[1] = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32) & 0xffffu);   // stride 0
-        // RAGGED: 2 GiB, all of whose valid offsets are in bounds.  Else no range clamp.
-        rsrc[2] = RAGGED ? 0x80000000u : 0xffffffffu;
+        rsrc[2] = RAGGED ? PAST : 0xffffffffu;   // else no range clamp: every offset is in bounds
         rsrc[3] = 0x00020000u;                   // raw 32-bit data format
         return rsrc;
     }
     // lds_stage: LDS byte address of this operand's tile in the destination stage;
-    // soff: byte advance of the stage along K inside the panel (wave-uniform).
-    // past: `past_end` in a panel's last stage, else 0
+    // soff: byte advance of the stage along K inside the panel (wave-uniform; RAGGED: zero, the
+    // descriptor has it)
     template <typename IT>
     __device__ __forceinline__ void request(IT it, const u32x4& rsrc, uint32_t lds_stage, int wave_u,
                                             uint32_t soff, uint32_t past) const
     {
-        const uint32_t voff = RAGGED ? off[it] | ((past << (31 - it)) & 0x80000000u) : off[it];
+        // sent(it, off[it], past) in two instructions (the compiler makes a test and a select of it, five)
+        uint32_t voff = off[it];
+        if constexpr (RAGGED)
+            asm("v_bfe_i32 %0, %1, %2, 1\n\tv_bfi_b32 %0, %0, %3, %4"
+                : "=&v"(voff) : "v"(past), "n"(it()), "s"(PAST), "v"(off[it]));
         // the descriptor must sit in scalar registers whatever the optimizer did to it
         u32x4 d;
         d[0] = __builtin_amdgcn_readfirstlane(rsrc[0]);
@@ -322,10 +361,11 @@ __global__ __launch_bounds__(64 * WGM * WGN) void tess_mfma_kernel(GemmArgs g)
     // State of the tile being requested (captured by aim(), so that the requests that
     // trickle out later do not see the pointers already advanced to the next tile).
     uint32_t rq_stage = 0;          // LDS address of the stage being filled
-    uint32_t rq_asoff = 0, rq_bsoff = 0;   // K advance of that tile inside its panels
+    uint32_t rq_asoff = 0, rq_bsoff = 0;   // K advance of that tile inside its panels (RAGGED: in the descriptors)
     uint32_t rq_apast = 0, rq_bpast = 0;   // RAGGED: requests of that tile that lie past the panel's end
     u32x4 rq_rsrc_a = {0u, 0u, 0u, 0u}, rq_rsrc_b = {0u, 0u, 0u, 0u};
     int rq_left = 0;                // tiles not yet aimed at
+    uint64_t rg_a = 0, rg_b = 0;    // RAGGED: the tile's first element in the panel aimed at
     auto request = [&](auto it) {
         if constexpr (it < LA::ITERS) la.request(it, rq_rsrc_a, rq_stage, wave_u, rq_asoff, rq_apast);
         else lb.request(std::integral_constant<int, it - LA::ITERS>{}, rq_rsrc_b, rq_stage + A_BYTES, wave_u, rq_bsoff, rq_bpast);
@@ -335,22 +375,33 @@ __global__ __launch_bounds__(64 * WGM * WGN) void tess_mfma_kernel(GemmArgs g)
     // every period then issues the same requests and the wait counts stay constant.
     auto aim = [&](int stage) {
         rq_stage = __builtin_amdgcn_readfirstlane(lds_base + stage * STAGE_BYTES);
-        rq_asoff = __builtin_amdgcn_readfirstlane(ld_ks * a_kstep);
-        rq_bsoff = __builtin_amdgcn_readfirstlane(ld_ks * b_kstep);
+        uint32_t a_adv = ld_ks * a_kstep, b_adv = ld_ks * b_kstep;
 #ifdef TESS_DBG_SAMEK
-        rq_asoff = rq_bsoff = 0;      // diagnostic build (wrong results): every stage re-reads K slice 0, so all requests hit the L2
+        a_adv = b_adv = 0;            // diagnostic build (wrong results): every stage re-reads K slice 0, so all requests hit the L2
 #endif
         if constexpr (RAGGED) {
             const bool last = ld_ks + 1 == kt_per_panel;
             rq_apast = last ? la.past_end : 0u;
             rq_bpast = last ? lb.past_end : 0u;
+            rq_rsrc_a = LA::descriptor(rg_a + a_adv);
+            rq_rsrc_b = LB::descriptor(rg_b + b_adv);
+        } else {
+            rq_asoff = __builtin_amdgcn_readfirstlane(a_adv);
+            rq_bsoff = __builtin_amdgcn_readfirstlane(b_adv);
+            const int t = ld_t < g.q ? ld_t : g.q - 1;
+            rq_rsrc_a = LA::descriptor((uint64_t)(uintptr_t)ka->a[t]);
+            rq_rsrc_b = LB::descriptor((uint64_t)(uintptr_t)ka->b[t]);
         }
-        const int t = ld_t < g.q ? ld_t : g.q - 1;
-        rq_rsrc_a = LA::descriptor(ka->a[t]);
-        rq_rsrc_b = LB::descriptor(ka->b[t]);
         if (rq_left > 1) {
             --rq_left;
-            if (++ld_ks == kt_per_panel) { ld_ks = 0; ++ld_t; }
+            if (++ld_ks == kt_per_panel) {
+                ld_ks = 0;
+                ++ld_t;
+                if constexpr (RAGGED) {
+                    rg_a = LA::start((uint64_t)(uintptr_t)ka->a[ld_t], row0, g.lda, 0u);
+                    rg_b = LB::start((uint64_t)(uintptr_t)ka->b[ld_t], col0, g.ldb, 0u);
+                }
+            }
         }
     };
     // with three or more stages a tile has more than a period to land and its requests
@@ -402,6 +453,9 @@ __global__ __launch_bounds__(64 * WGM * WGN) void tess_mfma_kernel(GemmArgs g)
             kt_begin = z * base + (z < extra ? z : extra);
             nkt = base + (z < extra ? 1 : 0);
         }
+        // in scalar registers, and with them all that goes into the descriptors (see DmaLoader)
+        tm = __builtin_amdgcn_readfirstlane(tm);
+        tn = __builtin_amdgcn_readfirstlane(tn);
         row0 = tm * BM;
         col0 = tn * BN;
         ld_t = kt_begin / kt_per_panel;
@@ -423,6 +477,10 @@ __global__ __launch_bounds__(64 * WGM * WGN) void tess_mfma_kernel(GemmArgs g)
         la.init(lane, wave_u, row0, g.M, g.lda, ktail);
         lb.init(lane, wave_u, col0, g.N, g.ldb, ktail);
         rq_left = nkt;
+        if constexpr (RAGGED) {
+            rg_a = LA::start((uint64_t)(uintptr_t)ka->a[ld_t], row0, g.lda, 0u);
+            rg_b = LB::start((uint64_t)(uintptr_t)ka->b[ld_t], col0, g.ldb, 0u);
+        }
         constexpr int FIRST = (FM * FN + STRIDE - 1) / STRIDE < LOADS ? (FM * FN + STRIDE - 1) / STRIDE : LOADS;
         if (nkt > 0) {
             // tiles 0 .. NSTAGE-2 in bulk, and of tile NSTAGE-1 the requests that the

@@ -74,6 +74,9 @@ __global__ __launch_bounds__(256) void tess_mfma_small_kernel(GemmArgs g)
         kt_begin = z * base + (z < extra ? z : extra);
         nkt = base + (z < extra ? 1 : 0);
     }
+    // in scalar registers, and with them all that goes into the descriptors (see DmaLoader)
+    tm = __builtin_amdgcn_readfirstlane(tm);
+    tn = __builtin_amdgcn_readfirstlane(tn);
     const int row0 = tm * BM, col0 = tn * BN;
 
     typedef DmaLoader<BM, BK, A_KC, 256, RAGGED> LA;
@@ -87,9 +90,11 @@ __global__ __launch_bounds__(256) void tess_mfma_small_kernel(GemmArgs g)
     const uint32_t b_kstep = B_KC ? (uint32_t)BK * 2 : (uint32_t)(BK * g.ldb * 2);
 
     // next stage to request; past the end the last one is requested again, so that the wait counts
-    // stay constant.  The descriptors change with the panel only.
+    // stay constant.  The descriptors change with the panel (RAGGED: the stage) only.
     int ld_t = kt_begin / kt_per_panel, ld_ks = kt_begin - ld_t * kt_per_panel, ld_left = nkt;
-    u32x4 rsrc_a = LA::descriptor(ka->a[ld_t]), rsrc_b = LB::descriptor(ka->b[ld_t]);
+    uint64_t from_a = LA::start((uint64_t)(uintptr_t)ka->a[ld_t], row0, g.lda, ld_ks * a_kstep);
+    uint64_t from_b = LB::start((uint64_t)(uintptr_t)ka->b[ld_t], col0, g.ldb, ld_ks * b_kstep);
+    u32x4 rsrc_a = LA::descriptor(from_a), rsrc_b = LB::descriptor(from_b);
     LA la;
     LB lb;
     const int ktail = g.Kp - (kt_per_panel - 1) * BK;
@@ -98,22 +103,32 @@ __global__ __launch_bounds__(256) void tess_mfma_small_kernel(GemmArgs g)
     uint32_t rq_stage = 0, rq_asoff = 0, rq_bsoff = 0, rq_apast = 0, rq_bpast = 0;
     auto aim = [&](int slot) {
         rq_stage = __builtin_amdgcn_readfirstlane(lds_base + slot * STAGE_BYTES);
-        rq_asoff = __builtin_amdgcn_readfirstlane(ld_ks * a_kstep);
-        rq_bsoff = __builtin_amdgcn_readfirstlane(ld_ks * b_kstep);
         if constexpr (RAGGED) {
             const bool last = ld_ks + 1 == kt_per_panel;
             rq_apast = last ? la.past_end : 0u;
             rq_bpast = last ? lb.past_end : 0u;
+        } else {
+            rq_asoff = __builtin_amdgcn_readfirstlane(ld_ks * a_kstep);
+            rq_bsoff = __builtin_amdgcn_readfirstlane(ld_ks * b_kstep);
         }
     };
     auto advance = [&] {        // behind the requests of the stage that was aimed at
         if (ld_left > 1) {
             --ld_left;
+            bool moved = RAGGED;
             if (++ld_ks == kt_per_panel) {
                 ld_ks = 0;
                 ++ld_t;
-                rsrc_a = LA::descriptor(ka->a[ld_t]);
-                rsrc_b = LB::descriptor(ka->b[ld_t]);
+                from_a = LA::start((uint64_t)(uintptr_t)ka->a[ld_t], row0, g.lda, 0u);
+                from_b = LB::start((uint64_t)(uintptr_t)ka->b[ld_t], col0, g.ldb, 0u);
+                moved = true;
+            } else if constexpr (RAGGED) {
+                from_a += a_kstep;
+                from_b += b_kstep;
+            }
+            if (moved) {
+                rsrc_a = LA::descriptor(from_a);
+                rsrc_b = LB::descriptor(from_b);
             }
         }
     };

@@ -197,6 +197,24 @@ def test_build_check_of_m0_writes():
     assert bld.check_m0_writes("s_lshl_b32 m0, s1, 2") != []
 
 
+def test_build_check_finds_requests_behind_vector_writes_of_their_scalars():
+    from paper_2105_14500_amd import build as bld
+    request = "buffer_load_dwordx4 v2, s[8:11], s12 offen offset:0x400 lds"
+    near = "v_readfirstlane_b32 s9, v3\n"
+    assert bld.check_request_scalars(near + request) != []
+    assert bld.check_request_scalars(near + "s_nop 3\n" + request) != [] and bld.check_request_scalars(near + "s_nop 4\n" + request) == []
+    assert bld.check_request_scalars("v_readfirstlane_b32 s12, v3\n" + request) != []           # the scalar offset
+    assert bld.check_request_scalars("v_cmp_ne_u32_e64 s[10:11], v1, v2\n" + request) != []
+    assert bld.check_request_scalars("v_mad_u64_u32 v[2:3], s[8:9], v4, v5, v[6:7]\n" + request) != []
+    assert bld.check_request_scalars("v_readfirstlane_b32 s13, v3\n" + request) == []
+    assert bld.check_request_scalars("v_add_u32_e32 v3, s9, v3\n" + request) == []                # reads it only
+    assert bld.check_request_scalars(near + "s_add_u32 s9, s9, 16\n" + request) == []            # a scalar write came last
+    # across a jump, and around a loop
+    assert bld.check_request_scalars(near + "s_branch .L1\ns_nop 7\n.L1:\n" + request) != []
+    assert bld.check_request_scalars(".L1:\n" + request + "\n" + near + "s_cbranch_scc0 .L1") != []
+    assert bld.check_request_scalars(near + "s_endpgm\n.L2:\n" + request) == []
+
+
 def test_partition_helpers_match_block_table():
     """Views produced for processor (i,j,k) are the blocks of the hand-written table
     tests/golden/partition_q2_d2.txt (Alg. 3, h = i + k*q)."""
