@@ -773,7 +773,17 @@ static hipError_t launch_tiles(const GemmArgs& g, const Plan& p, hipStream_t s)
         return launch_one<256, 256, 64, 2, 2, 2, A_KC, B_KC, false, COLSUM>(g, p, s);
     }
     if (p.bm == 128 && p.bn == 128) {
-        if (!p.direct) return launch_one<128, 128, 64, 3, 2, 2, A_KC, B_KC, true, COLSUM>(g, p, s);
+        if (!p.direct) {
+            // More workgroups than compute units: two stages, so that a compute unit holds two workgroups
+            // and one's start and drain overlap with the other's loop.  Up to one each, a third stage
+            // hides the loads' latency.  us a call (workgroups, stages of the contraction), 3 stages -> 2:
+            //   152 x 3632 x 4952 dW (1131, 3)  60.9 -> 42.8    4 x 184 x 1568 x 4864 dW (494, 12)  37.0 -> 27.2
+            //   2952 x 2152 x 72 dX  (408, 2)   12.2 ->  9.1    3 x 2520 x 2352 x 2776 fwd (440, 111)  132 -> 117
+            //   4 x 928 x 2168 x 3424 fwd (216, 136)  80.2, 120 with two    2 x 2240 x 128 x 1088 fwd (162, 4)  11.2, 11.9
+            const int64_t wgs = (int64_t)((g.M + 127) / 128) * ((g.N + 127) / 128) * (p.splits > 1 ? p.splits : 1);
+            if (wgs > 256) return launch_one<128, 128, 64, 2, 2, 2, A_KC, B_KC, true, COLSUM>(g, p, s);
+            return launch_one<128, 128, 64, 3, 2, 2, A_KC, B_KC, true, COLSUM>(g, p, s);
+        }
         return launch_one<128, 128, 64, 3, 2, 2, A_KC, B_KC, false, COLSUM>(g, p, s);
     }
     return hipErrorInvalidValue;

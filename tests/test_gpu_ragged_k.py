@@ -45,3 +45,35 @@ def test_stages_past_the_panel_end_read_as_zero(tile, splits, m, kb, n):
     assert np.array_equal(f64(dx), orc.bwd_dx_panels(dys, ws))
     assert np.array_equal(f64(dw), orc.bwd_dw_panels(xs, dys))
     assert np.array_equal(f64(db), sum(d.sum(0) for d in dys))
+
+
+@pytest.mark.parametrize("op", ["fwd", "dx", "dw"])
+@pytest.mark.parametrize("rows,cols,splits,k,q", [(2056, 2104, 1, 8, 1), (2056, 2104, 1, 72, 2), (2056, 2104, 1, 200, 3),
+                                                  (1544, 1672, 2, 72, 2), (1544, 1672, 2, 200, 3)])
+def test_more_workgroups_than_compute_units(op, rows, cols, splits, k, q):
+    """Two stages in the LDS in place of three, two workgroups per compute unit: 289 tiles, and 156 in two
+    parts; contractions of one stage, fewer stages than the ring holds, and more."""
+    m, kb, n = {"fwd": (rows, k, cols), "dx": (rows, cols, k), "dw": (k, rows, cols)}[op]
+    gen = torch.Generator().manual_seed(rows + k)
+    desc = share_desc(q, 1, m, kb, n, "bf16", "f32")
+    code = {"fwd": B.OP_FWD, "dx": B.OP_BWD_DX, "dw": B.OP_BWD_DW}[op]
+    out = torch.full((rows, cols), float("nan"), dtype=torch.float32, device="cuda:0")
+    first = _panels(q, *((m, n) if op == "dx" else (m, kb)), gen)
+    second = _panels(q, *((m, n) if op == "dw" else (kb, n)), gen)
+    db = torch.empty((n,), dtype=torch.float32, device="cuda:0")
+    try:
+        B.set_plan_override(tile=128, k_splits=splits)
+        assert tess.plan(desc, code) == (128, 128, splits)
+        ws = workspace(desc, code)
+        if op == "fwd":
+            tess.linear_fwd(desc, first[1], second[1], None, B.ACT_NONE, out, workspace=ws)
+        elif op == "dx":
+            tess.linear_bwd_dx(desc, first[1], second[1], out, workspace=ws)
+        else:
+            tess.linear_bwd_dw_bias(desc, first[1], second[1], out, db, workspace=ws)
+    finally:
+        B.set_plan_override(0, 0)
+    want = {"fwd": orc.fwd_panels, "dx": orc.bwd_dx_panels, "dw": orc.bwd_dw_panels}[op](first[0], second[0])
+    assert np.array_equal(f64(out), want)
+    if op == "dw":
+        assert np.array_equal(f64(db), sum(d.sum(0) for d in second[0]))

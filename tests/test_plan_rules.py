@@ -1,0 +1,18 @@
+"""Host-only: launch plans where the cost model alone chose a kernel that measures slower, one shape for
+each rule beside it (tess_api.cpp has both sides' times)."""
+import pytest
+
+from paper_2105_14500_amd import binding as B
+
+OPS = {"fwd": B.OP_FWD, "dx": B.OP_BWD_DX, "dw": B.OP_BWD_DW}
+
+
+def _plan(op, q, m, kb, n):
+    return B.plan(B.make_desc(q, 1, 0, 0, 0, m * q, kb * q, n * q, B.BF16, B.BF16), OPS[op])
+
+
+@pytest.mark.parametrize("op,q,m,kb,n,tile", [
+    ("dw", 1, 152, 3632, 4952, 128), ("fwd", 8, 4216, 16, 4840, 128), ("fwd", 3, 4992, 32, 3568, 128),      # few stages
+    ("fwd", 1, 2312, 3024, 4600, 256), ("dx", 4, 4032, 3160, 104, 256)])                                   # many, plain drain
+def test_256_tiles_of_ragged_contractions(op, q, m, kb, n, tile):
+    assert _plan(op, q, m, kb, n) == (tile, tile, 1)
