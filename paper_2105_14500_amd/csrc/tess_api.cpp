@@ -102,7 +102,16 @@ static Plan shape_plan(int64_t M, int64_t N, int64_t Kp, int q, bool in_bf16, bo
         for (int sp = 1; sp <= 16; ++sp) {
             if (sp > 1 && (kt_total / sp < 8 || ws_bytes(tiles, tc.bm, tc.bn, sp) > ws_limit)) break;
             const int64_t wgs = tiles * sp;
-            const double kt = (double)((kt_total + sp - 1) / sp);
+            // What the model does not see.  Few stages on more tiles than are resident at once (dX, whose drain
+            // is the shortest: than one per compute unit) are all starts and drains, of which the 128 x 128 tile
+            // has a quarter; the accumulating drain of dW alone is as long on either.  us, 64 x 64 / 128 x 128:
+            //   2304 x 2816 x 64 dX (1584 tiles)  18.9 / 10.8    4224 x 64 x 512 fwd (528)  12.4 / 10.1
+            //   3 x 2112 x 640 x 64 dX (330)       7.5 /  7.0    3 x 64 x 3968 x 1216 dW (1178)  21.4 / 24.9
+            if (wgs > (b_kc && p.direct && tc.bn == 64 ? 256 : 512) && kt_total < 8 && (a_kc || !p.direct)) break;
+            double kt = (double)((kt_total + sp - 1) / sp);
+            // and whole dW contractions of many stages, all of whose reads transpose (64 x 64 / 128 x 128 in parts):
+            //   8 x 704 x 1024 x 576 (88 stages)  25.7 / 21.2    5760 x 1472 x 576 (90)  26.9 / 24.5
+            if (!a_kc && p.direct && sp == 1 && kt_total >= 64) kt *= 1.15;
             const int64_t full_rounds = wgs / kCU, rem = wgs % kCU;
             double cost = kLaunchUs + tc.fixed_us + (double)full_rounds * (tc.round_us + stage * kt * tc.stage_full_us);
             if (rem) {

@@ -16,3 +16,12 @@ def _plan(op, q, m, kb, n):
     ("fwd", 1, 2312, 3024, 4600, 256), ("dx", 4, 4032, 3160, 104, 256)])                                   # many, plain drain
 def test_256_tiles_of_ragged_contractions(op, q, m, kb, n, tile):
     assert _plan(op, q, m, kb, n) == (tile, tile, 1)
+
+
+@pytest.mark.parametrize("op,q,m,kb,n,tile", [
+    ("dx", 1, 2304, 2816, 64, 128), ("dx", 3, 2112, 640, 64, 128), ("fwd", 1, 4224, 64, 512, 128),          # few stages, many tiles
+    ("dx", 2, 3616, 1296, 120, 128), ("dw", 1, 16, 1344, 3376, 128),
+    ("dw", 3, 64, 3968, 1216, 64), ("dx", 2, 1600, 640, 192, 64), ("fwd", 3, 5568, 128, 192, 64),           # the other side of the line
+    ("dw", 8, 704, 1024, 576, 128), ("dw", 1, 5760, 1472, 576, 128), ("dw", 8, 448, 1408, 704, 64)])        # many stages of dW
+def test_64_tiles(op, q, m, kb, n, tile):
+    assert _plan(op, q, m, kb, n)[0] == tile
