@@ -33,7 +33,14 @@ static hipError_t launch_any_type(const GemmArgs& g, hipStream_t s)
 {
     const int64_t tiles64 = (int64_t)((g.N + 63) / 64) * ((g.M + 63) / 64);
     constexpr bool F32 = sizeof(T) == 4;
-    if (tiles64 < (F32 ? 192 : 128)) return launch_any_tile<T, 32, 32, 256 / sizeof(T), 1, 1, 4>(g, s);
+    if (tiles64 < (F32 ? 192 : 128)) {
+        if constexpr (!F32) {
+            // panels shorter than a stage of 128 load element by element; us, stages of 128 / of 64 [scalar]:
+            //   11 x 17 x 17 dX  8.3 / 5.4 [5.6]    3775 x 15 x 13 dX  9.1 / 6.9 [7.0]    167 x 51 x 1465 fwd  10.2 / 8.3 [7.9]
+            if (g.Kp < 128) return launch_any_tile<T, 32, 32, 64, 1, 1, 4>(g, s);
+        }
+        return launch_any_tile<T, 32, 32, 256 / sizeof(T), 1, 1, 4>(g, s);
+    }
     if constexpr (F32) {
         if (tiles64 <= 512) return launch_any_tile<T, 64, 64, 64, 2, 2, 2>(g, s);
     }

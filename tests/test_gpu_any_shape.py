@@ -26,7 +26,7 @@ def _panels(q, rows, cols, dtype, gen):
 
 
 SIZES = [(1, 1, 1), (31, 33, 65), (32, 32, 64), (33, 64, 63), (65, 127, 129), (3, 200, 7), (300, 1, 5),
-         (63, 65, 257), (705, 33, 769), (704, 257, 768), (769, 700, 65),
+         (63, 65, 257), (45, 127, 33), (45, 129, 33), (127, 45, 129), (705, 33, 769), (704, 257, 768), (769, 700, 65),
          # 64 x 64 tiles of eight wavefronts (fp32 outputs of 192 to 512 tiles), one call each
          (833, 131, 1025), (961, 1025, 66), (70, 961, 897), (1023, 33, 769)]
 
