@@ -333,7 +333,7 @@ def _ws(workspace):
 def linear_fwd(desc, a_panels, b_panels, bias, act, c_out, preact_out=None, workspace=None,
                stream=None):
     """tess_linear_fwd: c_out = act(sum_t a_panels[t] @ b_panels[t] + bias)."""
-    st = _native().fwd(ctypes.addressof(desc), a_panels, b_panels, bias, act, c_out, preact_out, workspace, stream)
+    st = _native().fwd(ctypes.addressof(desc) if isinstance(desc, TessDesc) else None, a_panels, b_panels, bias, act, c_out, preact_out, workspace, stream)
     if st < 0:
         m, kb, n = block_shape(desc)
         _dtypes(a_panels=(desc.in_dtype, a_panels), b_panels=(desc.in_dtype, b_panels),
@@ -361,7 +361,7 @@ def linear_fwd(desc, a_panels, b_panels, bias, act, c_out, preact_out=None, work
 
 def linear_bwd_dx(desc, dy_panels, w_panels, dx_out, workspace=None, stream=None):
     """tess_linear_bwd_dx: dx_out = sum_t dy_panels[t] @ w_panels[t]^T."""
-    st = _native().dx(ctypes.addressof(desc), dy_panels, w_panels, dx_out, workspace, stream)
+    st = _native().dx(ctypes.addressof(desc) if isinstance(desc, TessDesc) else None, dy_panels, w_panels, dx_out, workspace, stream)
     if st < 0:
         m, kb, n = block_shape(desc)
         _dtypes(dy_panels=(desc.in_dtype, dy_panels), w_panels=(desc.in_dtype, w_panels),
@@ -378,7 +378,7 @@ def linear_bwd_dx(desc, dy_panels, w_panels, dx_out, workspace=None, stream=None
 
 def linear_bwd_dx_act(desc, dy_panels, w_panels, preact, act, dz_out, workspace=None, stream=None):
     """tess_linear_bwd_dx_act: dz_out = (sum_t dy_panels[t] @ w_panels[t]^T) * act'(preact)."""
-    st = _native().dx_act(ctypes.addressof(desc), dy_panels, w_panels, preact, act, dz_out, workspace, stream)
+    st = _native().dx_act(ctypes.addressof(desc) if isinstance(desc, TessDesc) else None, dy_panels, w_panels, preact, act, dz_out, workspace, stream)
     if st < 0:
         m, kb, n = block_shape(desc)
         _dtypes(dy_panels=(desc.in_dtype, dy_panels), w_panels=(desc.in_dtype, w_panels),
@@ -397,7 +397,7 @@ def linear_bwd_dx_act(desc, dy_panels, w_panels, preact, act, dz_out, workspace=
 def linear_bwd_dw_bias(desc, x_panels, dy_panels, dw_out, dbias_out, accumulate=False,
                        workspace=None, stream=None):
     """tess_linear_bwd_dw_bias: linear_bwd_dw plus dbias_out (+)= column sums of the dy panels."""
-    st = _native().dw_bias(ctypes.addressof(desc), x_panels, dy_panels, dw_out, accumulate, dbias_out, workspace, stream)
+    st = _native().dw_bias(ctypes.addressof(desc) if isinstance(desc, TessDesc) else None, x_panels, dy_panels, dw_out, accumulate, dbias_out, workspace, stream)
     if st < 0:
         m, kb, n = block_shape(desc)
         _dtypes(x_panels=(desc.in_dtype, x_panels), dy_panels=(desc.in_dtype, dy_panels),
@@ -451,7 +451,7 @@ def linear_bwd_dw_step(desc, x_block, dy_block, partial_out, accumulate=False, w
 def linear_bwd_dw(desc, x_panels, dy_panels, dw_out, accumulate=False, workspace=None,
                   stream=None):
     """tess_linear_bwd_dw: dw_out (+)= sum_t x_panels[t]^T @ dy_panels[t]."""
-    st = _native().dw(ctypes.addressof(desc), x_panels, dy_panels, dw_out, accumulate, workspace, stream)
+    st = _native().dw(ctypes.addressof(desc) if isinstance(desc, TessDesc) else None, x_panels, dy_panels, dw_out, accumulate, workspace, stream)
     if st < 0:
         m, kb, n = block_shape(desc)
         _dtypes(x_panels=(desc.in_dtype, x_panels), dy_panels=(desc.in_dtype, dy_panels),

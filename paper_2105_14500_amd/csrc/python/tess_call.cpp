@@ -2,7 +2,8 @@
 // looking each of them over from Python costs about 1 us apiece and made the host the slower side of
 // every call below some 30 us.
 //
-// Each function takes the address of the descriptor and the tensors as the Python caller has them.
+// Each function takes the address of the descriptor, or None where the caller was handed anything
+// but a TessDesc, and the tensors as the Python caller has them.
 // It returns the library's status when everything is plain (torch.Tensor and Parameter objects on the device,
 // the descriptor's types and shapes, contiguous rows, lists or tuples of q panels with one leading
 // dimension) and -1, with no call made, when anything is not: the Python code of binding.py then

@@ -185,6 +185,36 @@ def test_binding_refuses_tensors_of_the_wrong_dtype():
         B.linear_fwd(desc, x, w, None, B.ACT_NONE, torch.zeros(m, n, dtype=bf))
 
 
+def test_binding_takes_no_descriptor_but_a_tessdesc(monkeypatch):
+    """The native marshalling reads a whole descriptor at the address it is given: of anything else, a
+    structure with the same fields or a smaller object, it gets none, and the Python checks refuse it."""
+    import torch
+
+    class LooksAlike(ctypes.Structure):
+        _fields_ = B.TessDesc._fields_
+
+    given = []
+
+    class Native:
+        def __getattr__(self, name):
+            return lambda address, *rest: given.append(address) or -1
+
+    monkeypatch.setattr(B, "_native", Native)
+    t = torch.zeros(8, 8)
+    calls = (lambda d: B.linear_fwd(d, [t], [t], None, B.ACT_NONE, t), lambda d: B.linear_bwd_dx(d, [t], [t], t),
+             lambda d: B.linear_bwd_dx_act(d, [t], [t], t, B.ACT_NONE, t), lambda d: B.linear_bwd_dw(d, [t], [t], t),
+             lambda d: B.linear_bwd_dw_bias(d, [t], [t], t, t[0]))
+    for desc in (LooksAlike(1, 1, 0, 0, 0, 8, 8, 8, B.F32, B.F32), ctypes.c_int(1), (ctypes.c_int * 2)(1, 1)):
+        for call in calls:
+            with pytest.raises(ctypes.ArgumentError):
+                call(desc)
+    assert given == [None] * 15
+    desc = B.make_desc(1, 1, 0, 0, 0, 8, 8, 8, B.F32, B.F32)
+    with pytest.raises(ValueError, match="device"):
+        calls[0](desc)
+    assert given[-1] == ctypes.addressof(desc)
+
+
 def test_build_check_of_m0_writes():
     """The build refuses device code in which anything but the loader's own statement
     (s_mov_b32 m0 followed by s_nop 0) writes M0."""
