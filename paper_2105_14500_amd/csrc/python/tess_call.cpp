@@ -14,6 +14,7 @@
 #include <ATen/core/Tensor.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/utils/device_lazy_init.h>
 
 #include "tesseract.h"
 
@@ -115,6 +116,7 @@ Scratch scratch(PyObject* o)
 void* stream_of(PyObject* o)
 {
     need(o == Py_None);      // a stream object: its handle is read in Python
+    need(!torch::utils::is_device_in_bad_fork(at::kCUDA));      // refused there: no device call in a forked child
     return c10::hip::getCurrentHIPStream().stream();
 }
 

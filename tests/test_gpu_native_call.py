@@ -1,5 +1,7 @@
 """The two ways a linear call reaches the library: native marshalling for plain arguments and the
 Python checks for everything else, compared on the forms that decide between them."""
+import os
+
 import pytest
 import torch
 
@@ -71,3 +73,21 @@ def test_what_is_refused_stays_refused():
             tess.linear_fwd(desc, bad.get("x", x), w, bad.get("bias"), B.ACT_NONE, bad.get("y", y), preact_out=bad.get("z"))
     with pytest.raises(tess.TessError):
         tess.linear_fwd(desc, x, w, None, 7, y)
+
+
+def test_a_forked_child_is_refused():
+    """The runtime does not survive a fork: PyTorch refuses to name a stream in the child, and with the
+    stream left to the call so does every linear call, before any device call is made."""
+    desc = share_desc(1, 1, 16, 8, 8, "f32", "f32")
+    x, w, y = (torch.zeros(s, device="cuda:0") for s in ((16, 8), (8, 8), (16, 8)))
+    torch.cuda.synchronize()
+    child = os.fork()
+    if child == 0:
+        code = 1
+        try:
+            tess.linear_fwd(desc, [x], [w], None, B.ACT_NONE, y)
+        except RuntimeError as e:
+            code = 0 if "fork" in str(e) else 2
+        finally:
+            os._exit(code)
+    assert os.waitstatus_to_exitcode(os.waitpid(child, 0)[1]) == 0
