@@ -31,10 +31,12 @@ tess_status tess_probe_mfma_rate(void* sink, int32_t workgroups, int32_t iters, 
 tess_status tess_tile_of_block(int32_t block, int32_t tiles_m, int32_t tiles_n, int32_t* tm,
                                int32_t* tn);
 
-/* Forces the macro tile (128 or 256; 0 = cost model) and the number of equal K parts (>= 1;
+/* Forces the macro tile (128, 256 or one of the two below; 0 = cost model) and the number of equal K parts (>= 1;
  * 0 = cost model) of every later call of this process, where the shape allows them.
  * tess_linear_plan, tess_linear_workspace_bytes and the launches all see the same
  * override.  Process-wide and not synchronised with running calls: for sweeps and tests. */
+#define TESS_DIAG_TILE_64X64 64064
+#define TESS_DIAG_TILE_64X32 64032
 tess_status tess_diag_set_plan_override(int32_t tile, int32_t k_splits);
 
 #ifdef __cplusplus

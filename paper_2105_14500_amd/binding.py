@@ -202,8 +202,9 @@ def probe_mfma_rate(sink, workgroups, iters, real_data=False, stream=None):
 
 
 def set_plan_override(tile=0, k_splits=0):
-    """tess_diag_set_plan_override: force tile (128/256) and K splits of later calls; 0 = cost model."""
-    st = lib().tess_diag_set_plan_override(tile, k_splits)
+    """tess_diag_set_plan_override: force tile (128, 256, (64, 64) or (64, 32)) and K splits of later calls;
+    0 = cost model."""
+    st = lib().tess_diag_set_plan_override(tile[0] * 1000 + tile[1] if isinstance(tile, tuple) else tile, k_splits)
     if st:
         raise TessError(st, "tess_diag_set_plan_override")
 

@@ -125,7 +125,11 @@ static Plan shape_plan(int64_t M, int64_t N, int64_t Kp, int q, bool in_bf16, bo
     }
     // tuning overrides of the diagnostic interface; the workspace query, the plan query and
     // the launch all pass through here, so they agree
-    if (const int v = g_force_tile.load(std::memory_order_relaxed)) { if (v == 128 || (v == 256 && M >= 256 && N >= 256)) p.bm = p.bn = v; }
+    if (const int v = g_force_tile.load(std::memory_order_relaxed)) {
+        if (v == 128 || (v == 256 && M >= 256 && N >= 256)) p.bm = p.bn = v;
+        if (v == TESS_DIAG_TILE_64X64) p.bm = p.bn = 64;
+        if (v == TESS_DIAG_TILE_64X32) { p.bm = 64; p.bn = 32; }
+    }
     if (const int v = g_force_splits.load(std::memory_order_relaxed)) { if (v >= 1 && kt_total / v >= 1) { p.splits = v; } }
     const int64_t tiles = ((M + p.bm - 1) / p.bm) * ((N + p.bn - 1) / p.bn);
     p.ws_bytes = ws_bytes(tiles, p.bm, p.bn, p.splits);
@@ -538,7 +542,9 @@ tess_status tess_probe_mfma_rate(void* sink, int32_t workgroups, int32_t iters, 
 
 tess_status tess_diag_set_plan_override(int32_t tile, int32_t k_splits)
 {
-    if ((tile != 0 && tile != 128 && tile != 256) || k_splits < 0 || k_splits > 64) return TESS_ERR_UNSUPPORTED;
+    if (tile != 0 && tile != 128 && tile != 256 && tile != TESS_DIAG_TILE_64X64 && tile != TESS_DIAG_TILE_64X32)
+        return TESS_ERR_UNSUPPORTED;
+    if (k_splits < 0 || k_splits > 64) return TESS_ERR_UNSUPPORTED;
     g_force_tile.store(tile, std::memory_order_relaxed);
     g_force_splits.store(k_splits, std::memory_order_relaxed);
     return TESS_OK;

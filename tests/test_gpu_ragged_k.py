@@ -21,10 +21,17 @@ def _panels(q, rows, cols, gen):
     return [f64(h) for h in host], [room[t, :rows, :cols] for t in range(q)]
 
 
-@pytest.mark.parametrize("tile,splits", [(128, 1), (128, 3), (256, 1), (256, 2)])
-@pytest.mark.parametrize("m,kb,n", [(264, 328, 456), (312, 264, 376), (520, 1016, 264)])
+Q = 3
+TILES = [(128, 1), (128, 3), (256, 1), (256, 2)]
+SHAPES = [(264, 328, 456), (312, 264, 376), (520, 1016, 264)]
+# outputs of more than 256 workgroups: rows, columns, K parts, contraction of a panel, panels
+MANY = [(2056, 2104, 1, 8, 1), (2056, 2104, 1, 72, 2), (2056, 2104, 1, 200, 3), (1544, 1672, 2, 72, 2), (1544, 1672, 2, 200, 3)]
+
+
+@pytest.mark.parametrize("tile,splits", TILES)
+@pytest.mark.parametrize("m,kb,n", SHAPES)
 def test_stages_past_the_panel_end_read_as_zero(tile, splits, m, kb, n):
-    q = 3
+    q = Q
     gen = torch.Generator().manual_seed(tile + splits + m)
     desc = share_desc(q, 1, m, kb, n, "bf16", "f32")
     xs, xd = _panels(q, m, kb, gen)
@@ -48,8 +55,7 @@ def test_stages_past_the_panel_end_read_as_zero(tile, splits, m, kb, n):
 
 
 @pytest.mark.parametrize("op", ["fwd", "dx", "dw"])
-@pytest.mark.parametrize("rows,cols,splits,k,q", [(2056, 2104, 1, 8, 1), (2056, 2104, 1, 72, 2), (2056, 2104, 1, 200, 3),
-                                                  (1544, 1672, 2, 72, 2), (1544, 1672, 2, 200, 3)])
+@pytest.mark.parametrize("rows,cols,splits,k,q", MANY)
 def test_more_workgroups_than_compute_units(op, rows, cols, splits, k, q):
     """Two stages in the LDS in place of three, two workgroups per compute unit: 289 tiles, and 156 in two
     parts; contractions of one stage, fewer stages than the ring holds, and more."""

@@ -1,6 +1,9 @@
 """The 64 x 64 and 64 x 32 tiles of small outputs: remainders of the tiles, ragged panels, odd and
-even numbers of stages, K parts, every epilogue.  Products of small integers are exact in fp32 and must
-equal the fp64 oracle bit for bit."""
+even numbers of stages, K parts, every epilogue, on the plans of the cost model (which are 64 x 32 for
+nearly all of these shapes) and on each tile forced.  Products of small integers are exact in fp32 and
+must equal the fp64 oracle bit for bit."""
+import contextlib
+
 import numpy as np
 import pytest
 import torch
@@ -28,11 +31,39 @@ SHAPES = [(1, 64, 64, 64), (1, 8, 8, 8), (3, 72, 64, 40), (2, 64, 192, 96), (1, 
           (2, 512, 448, 520), (8, 64, 512, 256), (8, 256, 256, 256), (4, 64, 1024, 1032)]
 
 
+# (tile, K parts, (q, m, kb, n)): whole panels, then ragged ones in every call; with five stages or six
+# in the ring: fewer stages than that, one more, and many
+FORCED = [(tile, splits, shape) for tile in sorted(SMALL) for splits in (1, 3)
+          for shape in [(2, 192, 256, 320), (1, 192, 192, 192), (4, 448, 64, 128), (3, 136, 200, 264), (1, 136, 392, 152), (8, 72, 8, 104)]
+          if splits <= shape[0] * min(-(-k // 64) for k in shape[1:])]
+
+
+@contextlib.contextmanager
+def _forced(tile, splits):
+    try:
+        B.set_plan_override(tile=tile, k_splits=splits)
+        yield
+    finally:
+        B.set_plan_override(0, 0)
+
+
 @pytest.mark.parametrize("q,m,kb,n", SHAPES)
 def test_products_are_bit_exact(q, m, kb, n):
+    assert all(B.plan(share_desc(q, 1, m, kb, n, "bf16", "f32"), op)[:2] in SMALL for op in (B.OP_FWD, B.OP_BWD_DX, B.OP_BWD_DW))
+    _check_products(q, m, kb, n)
+
+
+@pytest.mark.parametrize("tile,splits,shape", FORCED)
+def test_products_are_bit_exact_on_every_tile(tile, splits, shape):
+    with _forced(tile, splits):
+        assert all(B.plan(share_desc(shape[0], 1, *shape[1:], "bf16", "f32"), op) == (*tile, splits)
+                   for op in (B.OP_FWD, B.OP_BWD_DX, B.OP_BWD_DW))
+        _check_products(*shape)
+
+
+def _check_products(q, m, kb, n):
     gen = torch.Generator().manual_seed(q + m + kb + n)
     desc = share_desc(q, 1, m, kb, n, "bf16", "f32")
-    assert all(B.plan(desc, op)[:2] in SMALL for op in (B.OP_FWD, B.OP_BWD_DX, B.OP_BWD_DW))
     xs, xd = _panels(q, m, kb, gen)
     ws, wd = _panels(q, kb, n, gen)
     dys, dyd = _panels(q, m, n, gen)
@@ -69,6 +100,19 @@ def test_forward_of_any_number_of_rows(m):
 @pytest.mark.parametrize("act", ["none", "gelu_erf", "gelu_tanh"])
 @pytest.mark.parametrize("pad", [0, 1])
 def test_epilogues(q, m, kb, n, out, act, pad):
+    _check_epilogues(q, m, kb, n, out, act, pad)
+
+
+@pytest.mark.parametrize("tile,splits", [(tile, splits) for tile in sorted(SMALL) for splits in (1, 2)])
+@pytest.mark.parametrize("out", ["bf16", "f32"])
+@pytest.mark.parametrize("act", ["none", "gelu_erf", "gelu_tanh"])
+@pytest.mark.parametrize("pad", [0, 1])
+def test_epilogues_of_every_tile(tile, splits, out, act, pad):
+    with _forced(tile, splits):
+        _check_epilogues(2, 136, 128, 200, out, act, pad)
+
+
+def _check_epilogues(q, m, kb, n, out, act, pad):
     gen = torch.Generator().manual_seed(q + pad)
     desc = share_desc(q, 1, m, kb, n, "bf16", out)
     odt = torch.bfloat16 if out == "bf16" else torch.float32

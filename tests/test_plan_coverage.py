@@ -1,8 +1,9 @@
 """Host-only: which kernel variant each shape of the GPU suite takes.  The launch plan is
 pure host arithmetic (tess_linear_plan), so this runs without a GPU and fails when a
 retuned cost model silently moves the GPU tests off a code path: every combination of
-{256 x 256 direct, 128 x 128 direct, 128 x 128 register-staged} x {no K split, K split} x
-{forward, input gradient, weight gradient} must be taken by at least one GPU test shape."""
+{256 x 256, 128 x 128 with three stages and with two, 64 x 64, 64 x 32} x {whole panels, ragged ones}
+x {no K split, K split} x {forward, input gradient, weight gradient} must be taken by at least one GPU
+test shape (the two-stage ring serves ragged panels only)."""
 import itertools
 
 import tess_workloads as wl
@@ -10,16 +11,22 @@ from paper_2105_14500_amd import binding as B
 
 import test_gpu_configs
 import test_gpu_parity
+import test_gpu_ragged_k
+import test_gpu_small_tiles
 import test_gpu_tile_grids
 
 
 def _variants(q, d, m, kb, n):
     desc = B.make_desc(q, d, 0, 0, 0, m * q * d, kb * q, n * q, B.BF16, B.BF16)
     out = []
-    for op, name, kp in ((B.OP_FWD, "fwd", kb), (B.OP_BWD_DX, "dx", n), (B.OP_BWD_DW, "dw", m)):
-        tile, _, splits = B.plan(desc, op)
-        if tile:
-            out.append(((tile, "direct" if kp % 64 == 0 else "staged"), "split" if splits > 1 else "whole", name))
+    for op, name, (M, N, kp) in ((B.OP_FWD, "fwd", (m, n, kb)), (B.OP_BWD_DX, "dx", (m, kb, n)), (B.OP_BWD_DW, "dw", (kb, n, m))):
+        bm, bn, splits = B.plan(desc, op)
+        if bm:
+            panels = "ragged" if kp % 64 else "whole"
+            tile = bm if bm == bn else (bm, bn)
+            if (tile, panels) == (128, "ragged") and -(-M // bm) * -(-N // bn) * splits > 256:
+                tile = "128 two stages"
+            out.append(((tile, panels), "split" if splits > 1 else "whole", name))
     return out
 
 
@@ -35,16 +42,26 @@ def test_gpu_suite_reaches_every_kernel_variant():
         for v in _variants(w.q, w.d, L.m, L.kb, L.n):
             seen.setdefault(v, ("test_gpu_configs.CASES", (wname, lname)))
     try:
-        for tile, splits, (q, d, m, kb, n) in test_gpu_parity.FORCED:
+        forced = [(t, s, shape, "test_gpu_parity.FORCED") for t, s, shape in test_gpu_parity.FORCED]
+        forced += [(t, s, (q, 1, *shape), "test_gpu_small_tiles.FORCED") for t, s, (q, *shape) in test_gpu_small_tiles.FORCED]
+        forced += [(t, s, (test_gpu_ragged_k.Q, 1, *shape), "test_gpu_ragged_k.TILES") for t, s in test_gpu_ragged_k.TILES
+                   for shape in test_gpu_ragged_k.SHAPES]
+        for tile, splits, shape, where in forced:
             B.set_plan_override(tile=tile, k_splits=splits)
-            for v in _variants(q, d, m, kb, n):
-                assert v[0][0] == tile and (v[1] == "split") == (splits > 1)
-                seen.setdefault(v, ("test_gpu_parity.FORCED", (tile, splits, q, d, m, kb, n)))
+            for v in _variants(*shape):
+                assert v[0][0] == (64 if tile == (64, 64) else tile) and (v[1] == "split") == (splits > 1)
+                seen.setdefault(v, (where, (tile, splits, shape)))
+        for rows, cols, splits, k, q in test_gpu_ragged_k.MANY:
+            B.set_plan_override(tile=128, k_splits=splits)
+            for name, shape in (("fwd", (rows, k, cols)), ("dx", (rows, cols, k)), ("dw", (k, rows, cols))):
+                for v in _variants(q, 1, *shape):
+                    if v[2] == name:
+                        seen.setdefault(v, ("test_gpu_ragged_k.MANY", (splits, q, shape)))
     finally:
         B.set_plan_override(0, 0)
-    want = set(itertools.product([(256, "direct"), (128, "direct"), (128, "staged")], ["whole", "split"],
-                                 ["fwd", "dx", "dw"]))
-    missing = sorted(want - set(seen))
+    tiles = list(itertools.product([256, 128, 64, (64, 32)], ["whole", "ragged"])) + [("128 two stages", "ragged")]
+    want = set(itertools.product(tiles, ["whole", "split"], ["fwd", "dx", "dw"]))
+    missing = sorted(want - set(seen), key=str)
     assert not missing, missing
 
 
