@@ -29,7 +29,8 @@
  *    host without a GPU; on a non-OK status no output has been touched.
  *  - Inputs must not alias outputs.  q <= TESS_MAX_Q.
  *  - in_dtype TESS_BF16 computes bf16 x bf16 products on the matrix cores with
- *    fp32 accumulation over all q steps; TESS_F32 uses fp32 fused multiply-add.
+ *    fp32 accumulation over all q steps; TESS_F32 computes with full fp32 operands and
+ *    fp32 accumulation, on the matrix cores too.
  *    Down-casts to bf16 round to nearest, ties to even.
  *  - Results are deterministic run to run (no floating-point atomics).
  */
@@ -237,11 +238,11 @@ size_t tess_linear_workspace_bytes(const tess_desc* desc, int op);
  * number of K splits (1 = the whole q-step sum stays in one workgroup's registers; > 1 =
  * that many equal parts of the K range, whose partial sums go through the workspace and are
  * added in ascending K order by a reduction kernel that applies the epilogue).  tile 0 x 0
- * means the plain
- * fp32 kernel: fp32 inputs, or a bf16 block whose contiguous extents are no multiple of 8.
- * Pure host arithmetic.  A call whose plan uses the matrix cores needs 16-byte aligned
+ * means the any-shape kernel, which picks its tiles by itself: fp32 inputs, or a bf16 block whose
+ * contiguous extents are no multiples of 8.
+ * Pure host arithmetic.  A call whose plan has a tile needs 16-byte aligned
  * panel pointers and leading dimensions that are multiples of 8 elements, and returns
- * TESS_ERR_ALIGN otherwise (it never drops to the plain kernel silently); a panel of 4 GiB
+ * TESS_ERR_ALIGN otherwise (it never drops to the any-shape kernel silently); a panel of 4 GiB
  * or more returns TESS_ERR_UNSUPPORTED. */
 tess_status tess_linear_plan(const tess_desc* desc, int op, int32_t* tile_m, int32_t* tile_n,
                              int32_t* k_splits);

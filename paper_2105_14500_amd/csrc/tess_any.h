@@ -2,7 +2,7 @@
 // multiples of 8: any shape, stride and element alignment, no workspace.
 //
 // Products run on v_mfma_f32_32x32x2_f32 (fp32: 256 flop/clk per compute unit, twice the unpacked
-// vector rate, exact fp32 products and sums) or v_mfma_f32_32x32x16_bf16.  Operand tiles go through
+// vector rate, full fp32 operands and fp32 accumulation) or v_mfma_f32_32x32x16_bf16.  Operand tiles go through
 // registers into a double-buffered LDS tile; the loads of a stage are issued two stages ahead.
 //
 // No edge is loaded element by element as long as the extents reach one tile and one stage: the

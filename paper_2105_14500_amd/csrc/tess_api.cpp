@@ -26,7 +26,7 @@ static Plan shape_plan(int64_t M, int64_t N, int64_t Kp, int q, bool in_bf16, bo
     p.ws_bytes = 0;
     if (!in_bf16) return p;
     // the matrix-core path moves 16-byte granules (8 bf16) along the contiguous index of
-    // each operand: extents that are no multiple of 8 take the plain kernel
+    // each operand: extents that are no multiple of 8 take the any-shape kernel
     if (a_kc ? (Kp % 8 != 0) : (M % 8 != 0)) return p;
     if (b_kc ? (Kp % 8 != 0) : (N % 8 != 0)) return p;
     p.path = Path::Mfma;
@@ -138,7 +138,7 @@ static Plan shape_plan(int64_t M, int64_t N, int64_t Kp, int q, bool in_bf16, bo
 
 // Plan of a launch with its operands: the shape plan, refused when the matrix-core path
 // that the shape selects cannot take these pointers or leading dimensions (a silent drop
-// to the plain kernel would be orders of magnitude slower than what tess_linear_plan says).
+// to the any-shape kernel would be several times slower than what tess_linear_plan says).
 static tess_status make_plan(const GemmArgs& g, Plan& p)
 {
     p = shape_plan(g.M, g.N, g.Kp, g.q, !g.in_f32, g.a_kc != 0, g.b_kc != 0);

@@ -19,7 +19,6 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 #define LDS_PTR(T) __attribute__((address_space(3))) T*
-#define GLB_PTR(T) __attribute__((address_space(1))) T*
 
 
 // Compile-time loop: the body sees the index as an integral constant, so every
@@ -101,14 +100,6 @@ __device__ __forceinline__ float apply_act(float z, int act)
     if (act == TESS_ACT_GELU_ERF) return gelu_erf_f(z);
     if (act == TESS_ACT_GELU_TANH) return gelu_tanh_f(z);
     return z;
-}
-// fp32 -> bf16 bits, round to nearest even (NaN kept quiet)
-__device__ __forceinline__ uint16_t f32_to_bf16_bits(float x)
-{
-    uint32_t u = __float_as_uint(x);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40u);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
 }
 __device__ __forceinline__ float bf16_bits_to_f32(uint16_t b)
 {

@@ -86,7 +86,7 @@ def test_workspace_query_and_enforcement():
     need = B.workspace_bytes(d, B.OP_FWD)
     assert need > 0 and need % 4 == 0
     assert B.workspace_bytes(d, 7) == 0
-    # fp32 problems use the plain kernel: no scratch
+    # fp32 problems use the any-shape kernel: no scratch
     d32 = B.make_desc(2, 1, 0, 0, 0, 256, 256, 1024, B.F32, B.F32)
     assert [B.workspace_bytes(d32, op) for op in (0, 1, 2)] == [0, 0, 0]
     L = B.lib()
@@ -103,7 +103,7 @@ def test_workspace_query_and_enforcement():
 
 def test_misaligned_bf16_operands_are_refused_not_rerouted():
     """A bf16 block whose shape selects the matrix-core kernel must not drop silently to the
-    plain fp32 kernel when a pointer or a leading dimension is misaligned."""
+    any-shape kernel when a pointer or a leading dimension is misaligned."""
     L = B.lib()
     d = B.make_desc(2, 2, 0, 0, 0, 64 * 4, 64 * 2, 64 * 2, B.BF16, B.BF16)
     assert B.plan(d, B.OP_FWD)[0] > 0
@@ -117,7 +117,7 @@ def test_misaligned_bf16_operands_are_refused_not_rerouted():
     assert L.tess_linear_bwd_dx(ref(d), ok, 64, odd, 64, out, 64, None, 0, None) == 4
     assert L.tess_linear_bwd_dw(ref(d), odd, 64, ok, 64, out, 64, 0, None, 0, None) == 4
     assert B.status_string(4) == "TESS_ERR_ALIGN"
-    # a block whose extents are no multiple of 8 is planned for the plain kernel (tile 0 x 0),
+    # a block whose extents are no multiple of 8 is planned for the any-shape kernel (tile 0 x 0),
     # which takes any alignment: the plan says so up front
     ragged = B.make_desc(2, 2, 0, 0, 0, 33 * 4, 17 * 2, 29 * 2, B.BF16, B.BF16)
     assert B.plan(ragged, B.OP_FWD) == (0, 0, 1) and B.plan(ragged, B.OP_BWD_DW) == (0, 0, 1)

@@ -21,18 +21,18 @@ pytestmark = pytest.mark.gpu
 SHAPES = [
     (2, 1, 256, 128, 256, "bf16"),    # direct 128x128 tiles, fwd split
     (2, 2, 512, 256, 512, "bf16"),    # several 128-tiles per side
-    (3, 2, 200, 72, 136, "bf16"),     # ragged M/N/K tails, register-staged loader
+    (3, 2, 200, 72, 136, "bf16"),     # ragged M/N/K tails
     (2, 2, 264, 64, 520, "bf16"),     # K % 64 == 0 (direct), ragged M and N
     (1, 1, 128, 192, 128, "bf16"),    # q = d = 1: plain matmul
     (4, 3, 40, 8, 16, "bf16"),        # tiny: one partial tile
-    (2, 2, 33, 17, 29, "bf16"),       # no 8-alignment: generic kernel, bf16 inputs
-    (2, 2, 130, 70, 100, "f32"),      # fp32 generic kernel, ragged
+    (2, 2, 33, 17, 29, "bf16"),       # no 8-alignment: any-shape kernel, bf16 inputs
+    (2, 2, 130, 70, 100, "f32"),      # any-shape kernel in fp32, ragged
     (3, 1, 64, 64, 64, "f32"),
     (2, 2, 1024, 1024, 1024, "bf16"),  # 256x256 tiles
     (2, 1, 2048, 256, 2048, "bf16"),   # 256x256 tiles, many of them
     (16, 1, 64, 64, 128, "bf16"),      # the largest grid dimension the ABI takes: 16 panels per operand
     (8, 8, 128, 64, 256, "bf16"),      # d = q (the 3-D end of the family)
-    (16, 2, 24, 40, 56, "f32"),        # 16 panels through the fp32 kernel
+    (16, 2, 24, 40, 56, "f32"),        # 16 panels through the any-shape kernel
 ]
 
 
@@ -62,7 +62,7 @@ def test_small_integers_are_bit_exact(q, d, m, kb, n, dtype):
 # diagnostic override: (tile, K splits, (q, d, m, kb, n)).  tests/test_plan_coverage.py checks
 # on the host that, with these, every kernel variant x split / no split x call is exercised.
 FORCED = [
-    (128, 3, (3, 2, 200, 72, 136)),        # register-staged loader (ragged K) with K splits
+    (128, 3, (3, 2, 200, 72, 136)),        # ragged K with K splits
     (128, 1, (2, 2, 264, 64, 520)),
     (128, 1, (2, 2, 264, 72, 520)),
     (256, 2, (2, 2, 1024, 1024, 1024)),    # 256 x 256 tiles, K split, several tiles
@@ -289,7 +289,7 @@ def _random_shapes(count, seed):
     for _ in range(count):
         q = int(r.integers(1, 6))
         d = int(r.integers(1, q + 1))
-        # multiples of 8 (MFMA path, ragged tiles) with an occasional odd size (fp32-FMA path)
+        # multiples of 8 (MFMA path, ragged tiles) with an occasional odd size (any-shape path)
         dims = [int(r.integers(1, 90)) * 8 for _ in range(3)]
         if r.random() < 0.2:
             dims[int(r.integers(0, 3))] += int(r.integers(1, 8))
