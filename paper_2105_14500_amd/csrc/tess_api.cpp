@@ -88,8 +88,9 @@ static Plan shape_plan(int64_t M, int64_t N, int64_t Kp, int q, bool in_bf16, bo
     // and where the line goes against them:
     //   2048 x 2048, K 1024, forward   17.8 (1), 23.9 with 64 x 64 tiles
     //   512 x 768, K 9216, dX          17.5 (9), 20.2 with 64 x 64 tiles in 2 parts
-    // Over those calls, each on operands that left the L2 since the last one, the choice is 1.28 times
-    // as fast as the larger tiles alone and 1 % above the best of all plans.
+    // Over 240 other random calls, each on operands that left the L2 since the last one, the choice is
+    // 1.30 times as fast as the best plan of the larger tiles and level with the best of all plans (20
+    // calls are more than 5 % above it, the worst 16 %).
     // A plan of small tiles never needs more workspace than the plan it takes the place of.
     struct SmallCost { int bm, bn; double fixed_us, stage_idle_us, stage_full_us, round_us; };
     const SmallCost small[2] = {{64, 64, 2.65, 0.080, 0.265, 1.04}, {64, 32, 0.45, 0.125, 0.200, 1.9}};
