@@ -113,10 +113,9 @@ Scratch scratch(PyObject* o)
     return {t.data_ptr(), (size_t)t.numel() * t.element_size()};
 }
 
-void* stream_of(PyObject* o)
+void* current_stream()
 {
-    need(o == Py_None);      // a stream object: its handle is read in Python
-    need(!torch::utils::is_device_in_bad_fork(at::kCUDA));      // refused there: no device call in a forked child
+    need(!torch::utils::is_device_in_bad_fork(at::kCUDA));      // Python refuses: no device call in a forked child
     return c10::hip::getCurrentHIPStream().stream();
 }
 
@@ -167,6 +166,7 @@ int released(F&& call)
 PyObject* fwd(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
     return guarded(n, 9, [&] {
+        if (a[8] != Py_None) return -1;      // a stream object: its handle is read in Python
         const Dims s = dims_of(a[0]);
         const Panels x = panels(a[1], s.d->q, s.d->in_dtype, s.m, s.kb), w = panels(a[2], s.d->q, s.d->in_dtype, s.kb, s.n);
         const void* bias = vec(a[3], scalar(s.d->in_dtype), s.n);
@@ -176,7 +176,7 @@ PyObject* fwd(PyObject*, PyObject* const* a, Py_ssize_t n)
         void* pre = a[6] == Py_None ? nullptr : block(a[6], s.d->out_dtype, s.m, s.n, ldp);
         need(!pre || ldp == ldc);
         const Scratch ws = scratch(a[7]);
-        void* st = stream_of(a[8]);
+        void* st = current_stream();
         return released([&] { return (int)entry.fwd(s.d, x.p, x.ld, w.p, w.ld, bias, act, out, ldc, pre, ws.p, ws.bytes, st); });
     });
 }
@@ -185,12 +185,13 @@ PyObject* fwd(PyObject*, PyObject* const* a, Py_ssize_t n)
 PyObject* dx(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
     return guarded(n, 6, [&] {
+        if (a[5] != Py_None) return -1;      // a stream object: its handle is read in Python
         const Dims s = dims_of(a[0]);
         const Panels dy = panels(a[1], s.d->q, s.d->in_dtype, s.m, s.n), w = panels(a[2], s.d->q, s.d->in_dtype, s.kb, s.n);
         int64_t ldo;
         void* out = block(a[3], s.d->out_dtype, s.m, s.kb, ldo);
         const Scratch ws = scratch(a[4]);
-        void* st = stream_of(a[5]);
+        void* st = current_stream();
         return released([&] { return (int)entry.dx(s.d, dy.p, dy.ld, w.p, w.ld, out, ldo, ws.p, ws.bytes, st); });
     });
 }
@@ -199,6 +200,7 @@ PyObject* dx(PyObject*, PyObject* const* a, Py_ssize_t n)
 PyObject* dx_act(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
     return guarded(n, 8, [&] {
+        if (a[7] != Py_None) return -1;      // a stream object: its handle is read in Python
         const Dims s = dims_of(a[0]);
         const Panels dy = panels(a[1], s.d->q, s.d->in_dtype, s.m, s.n), w = panels(a[2], s.d->q, s.d->in_dtype, s.kb, s.n);
         int64_t ldz, ldo;
@@ -206,7 +208,7 @@ PyObject* dx_act(PyObject*, PyObject* const* a, Py_ssize_t n)
         const int act = integer(a[4]);
         void* out = block(a[5], s.d->out_dtype, s.m, s.kb, ldo);
         const Scratch ws = scratch(a[6]);
-        void* st = stream_of(a[7]);
+        void* st = current_stream();
         return released([&] { return (int)entry.dx_act(s.d, dy.p, dy.ld, w.p, w.ld, z, ldz, act, out, ldo, ws.p, ws.bytes, st); });
     });
 }
@@ -236,9 +238,10 @@ DwArgs dw_args(PyObject* const* a)
 PyObject* dw(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
     return guarded(n, 7, [&] {
+        if (a[6] != Py_None) return -1;      // a stream object: its handle is read in Python
         const DwArgs r = dw_args(a);
         const Scratch ws = scratch(a[5]);
-        void* st = stream_of(a[6]);
+        void* st = current_stream();
         return released([&] { return (int)entry.dw(r.s.d, r.x.p, r.x.ld, r.dy.p, r.dy.ld, r.out, r.ldo, r.accumulate, ws.p, ws.bytes, st); });
     });
 }
@@ -247,10 +250,11 @@ PyObject* dw(PyObject*, PyObject* const* a, Py_ssize_t n)
 PyObject* dw_bias(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
     return guarded(n, 8, [&] {
+        if (a[7] != Py_None) return -1;      // a stream object: its handle is read in Python
         const DwArgs r = dw_args(a);
         void* db = vec(a[5], at::kFloat, r.s.n);
         const Scratch ws = scratch(a[6]);
-        void* st = stream_of(a[7]);
+        void* st = current_stream();
         return released([&] { return (int)entry.dw_bias(r.s.d, r.x.p, r.x.ld, r.dy.p, r.dy.ld, r.out, r.ldo, db, r.accumulate, ws.p, ws.bytes, st); });
     });
 }

@@ -75,6 +75,24 @@ def test_what_is_refused_stays_refused():
         tess.linear_fwd(desc, x, w, None, 7, y)
 
 
+def test_a_call_with_a_stream_is_turned_down_at_once():
+    """What the Python code will serve is not looked over twice: the activation code is asked for its value
+    once, by the Python call."""
+
+    class Act:
+        asked = 0
+
+        def __index__(self):
+            self.asked += 1
+            return B.ACT_NONE
+
+    desc = share_desc(1, 1, 16, 8, 8, "f32", "f32")
+    x, w, y = torch.ones((16, 8), device="cuda:0"), torch.ones((8, 8), device="cuda:0"), torch.zeros((16, 8), device="cuda:0")
+    act = Act()
+    tess.linear_fwd(desc, [x], [w], None, act, y, stream=torch.cuda.current_stream())
+    assert act.asked == 1 and torch.equal(y, torch.full_like(y, 8.0))
+
+
 def test_a_forked_child_is_refused():
     """The runtime does not survive a fork: PyTorch refuses to name a stream in the child, and with the
     stream left to the call so does every linear call, before any device call is made."""
