@@ -142,12 +142,12 @@ struct DmaLoader {
         const uint32_t mask = (uint32_t)((int32_t)(past << (31 - it)) >> 31);
         return (mask & PAST) | (~mask & off);
     }
-    // where the descriptor of a stage starts, less BIAS: in the panel at `panel`, the tile at row or
-    // column `origin`, `adv` bytes along K
+    // where the descriptor of a stage starts: in the panel at `panel`, the tile at row or column
+    // `origin`, `adv` bytes along K.  A later stage of the panel starts that many bytes on.
     static __host__ __device__ __forceinline__ uint64_t start(uint64_t panel, int origin, int64_t ld, uint32_t adv)
     {
-        if (!RAGGED) return panel;
-        return panel + (uint64_t)(KC ? origin * ld : origin) * 2 + adv;
+        if (RAGGED) panel += (uint64_t)(KC ? origin * ld : origin) * 2 + adv;
+        return (panel - BIAS) & 0xffffffffffffull;
     }
 
     // ktail: contracted elements of a panel's last stage
@@ -164,10 +164,9 @@ struct DmaLoader {
     // buffer descriptor of a panel, RAGGED: of one stage (kept by the caller in scalar registers)
     static __device__ __forceinline__ u32x4 descriptor(uint64_t from)
     {
-        const uint64_t base = from - BIAS;
         u32x4 rsrc;
-        rsrc[0] = __builtin_amdgcn_readfirstlane((uint32_t)base);
-        rsrc[1] = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32) & 0xffffu);   // stride 0
+        rsrc[0] = __builtin_amdgcn_readfirstlane((uint32_t)from);
+        rsrc[1] = __builtin_amdgcn_readfirstlane((uint32_t)(from >> 32));   // stride 0
         rsrc[2] = RAGGED ? PAST : 0xffffffffu;   // else no range clamp: every offset is in bounds
         rsrc[3] = 0x00020000u;                   // raw 32-bit data format
         return rsrc;
@@ -365,7 +364,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void tess_mfma_kernel(GemmArgs g)
     uint32_t rq_apast = 0, rq_bpast = 0;   // RAGGED: requests of that tile that lie past the panel's end
     u32x4 rq_rsrc_a = {0u, 0u, 0u, 0u}, rq_rsrc_b = {0u, 0u, 0u, 0u};
     int rq_left = 0;                // tiles not yet aimed at
-    uint64_t rg_a = 0, rg_b = 0;    // RAGGED: the tile's first element in the panel aimed at
+    uint64_t rg_a = 0, rg_b = 0;    // RAGGED: where the next stage's descriptors start
     auto request = [&](auto it) {
         if constexpr (it < LA::ITERS) la.request(it, rq_rsrc_a, rq_stage, wave_u, rq_asoff, rq_apast);
         else lb.request(std::integral_constant<int, it - LA::ITERS>{}, rq_rsrc_b, rq_stage + A_BYTES, wave_u, rq_bsoff, rq_bpast);
@@ -375,22 +374,21 @@ __global__ __launch_bounds__(64 * WGM * WGN) void tess_mfma_kernel(GemmArgs g)
     // every period then issues the same requests and the wait counts stay constant.
     auto aim = [&](int stage) {
         rq_stage = __builtin_amdgcn_readfirstlane(lds_base + stage * STAGE_BYTES);
-        uint32_t a_adv = ld_ks * a_kstep, b_adv = ld_ks * b_kstep;
-#ifdef TESS_DBG_SAMEK
-        a_adv = b_adv = 0;            // diagnostic build (wrong results): every stage re-reads K slice 0, so all requests hit the L2
-#endif
         if constexpr (RAGGED) {
             const bool last = ld_ks + 1 == kt_per_panel;
             rq_apast = last ? la.past_end : 0u;
             rq_bpast = last ? lb.past_end : 0u;
-            rq_rsrc_a = LA::descriptor(rg_a + a_adv);
-            rq_rsrc_b = LB::descriptor(rg_b + b_adv);
+            rq_rsrc_a = LA::descriptor(rg_a);
+            rq_rsrc_b = LB::descriptor(rg_b);
         } else {
-            rq_asoff = __builtin_amdgcn_readfirstlane(a_adv);
-            rq_bsoff = __builtin_amdgcn_readfirstlane(b_adv);
+            rq_asoff = __builtin_amdgcn_readfirstlane(ld_ks * a_kstep);
+            rq_bsoff = __builtin_amdgcn_readfirstlane(ld_ks * b_kstep);
+#ifdef TESS_DBG_SAMEK
+            rq_asoff = rq_bsoff = 0;      // diagnostic build (wrong results): every stage re-reads K slice 0, so all requests hit the L2
+#endif
             const int t = ld_t < g.q ? ld_t : g.q - 1;
-            rq_rsrc_a = LA::descriptor((uint64_t)(uintptr_t)ka->a[t]);
-            rq_rsrc_b = LB::descriptor((uint64_t)(uintptr_t)ka->b[t]);
+            rq_rsrc_a = LA::descriptor(LA::start((uint64_t)(uintptr_t)ka->a[t], row0, g.lda, 0u));
+            rq_rsrc_b = LB::descriptor(LB::start((uint64_t)(uintptr_t)ka->b[t], col0, g.ldb, 0u));
         }
         if (rq_left > 1) {
             --rq_left;
@@ -401,6 +399,9 @@ __global__ __launch_bounds__(64 * WGM * WGN) void tess_mfma_kernel(GemmArgs g)
                     rg_a = LA::start((uint64_t)(uintptr_t)ka->a[ld_t], row0, g.lda, 0u);
                     rg_b = LB::start((uint64_t)(uintptr_t)ka->b[ld_t], col0, g.ldb, 0u);
                 }
+            } else if constexpr (RAGGED) {
+                rg_a += a_kstep;
+                rg_b += b_kstep;
             }
         }
     };
@@ -478,8 +479,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void tess_mfma_kernel(GemmArgs g)
         lb.init(lane, wave_u, col0, g.N, g.ldb, ktail);
         rq_left = nkt;
         if constexpr (RAGGED) {
-            rg_a = LA::start((uint64_t)(uintptr_t)ka->a[ld_t], row0, g.lda, 0u);
-            rg_b = LB::start((uint64_t)(uintptr_t)ka->b[ld_t], col0, g.ldb, 0u);
+            rg_a = LA::start((uint64_t)(uintptr_t)ka->a[ld_t], row0, g.lda, ld_ks * a_kstep);
+            rg_b = LB::start((uint64_t)(uintptr_t)ka->b[ld_t], col0, g.ldb, ld_ks * b_kstep);
         }
         constexpr int FIRST = (FM * FN + STRIDE - 1) / STRIDE < LOADS ? (FM * FN + STRIDE - 1) / STRIDE : LOADS;
         if (nkt > 0) {

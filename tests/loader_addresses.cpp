@@ -28,7 +28,7 @@ static void check(int64_t extent, int64_t Kp, int64_t ld)
             if (tile < 0) continue;
             const int origin = (int)(tile * R);
             const uint32_t adv = (uint32_t)ks * (KC ? 128u : (uint32_t)(64 * ld * 2));
-            const uint64_t base = L::start(panel, origin, ld, adv) - L::BIAS;
+            const uint64_t base = L::start(panel, origin, ld, adv);
             for (int G = 0; G < R * 8; ++G) {
                 const int it = G / 64 % L::ITERS, imm = it % 4 * 1024;      // wavefront w: granules from w * ITERS * 64
                 int kpos;
