@@ -51,13 +51,15 @@ static Plan shape_plan(int64_t M, int64_t N, int64_t Kp, int q, bool in_bf16, bo
         const TileCost& tc = cands[ci];
         const int t = tc.t;
         if (t == 256 && !(M >= 256 && N >= 256)) continue;
-        // ragged contractions of few stages: the drain of 256 x 256 tiles (bias, GELU, accumulation) overlaps
-        // with nothing, two workgroups of 128 x 128 per compute unit cover each other's.  us a call, 256 / 128:
-        //   152 x 3632 x 4952 dW (3 stages)  71.3 / 42.8    8 x 4216 x 16 x 4840 fwd (8)  57.9 / 44.4
-        //   3 x 472 x 2752 x 4464 dW (24)    67.8 / 66.2    2312 x 3024 x 4600 fwd (48)   83.9 / 107.5
-        // and the plain drain of dX:  4 x 4032 x 3160 x 104 (8)  23.1 / 27.8
-        if (t == 256 && !p.direct && !b_kc && kt_total < 24) continue;
         const int64_t tiles = ((M + t - 1) / t) * ((N + t - 1) / t);
+        // Ragged contractions: the drain of 256 x 256 tiles (bias and GELU, accumulation) overlaps with nothing,
+        // where two workgroups of 128 x 128 per compute unit cover each other's, and half a second round of them
+        // costs a whole one.  us a call, 256 / 128 (stages, 256 x 256 tiles):
+        //   fwd  25.8 / 23.4 (4, 135)   29.8 / 29.5 (7, 154)   48.3 / 57.9 (19, 210)   50.5 / 59.1 (24, 140)
+        //   dW   39.1 / 29.8 (4, 144)   59.3 / 56.6 (18, 189)  63.4 / 63.0 (22, 176)   68.2 / 69.6 (26, 192)
+        //   dX   23.1 / 27.8 (8, 208)   15.4 / 15.0 (1, 247)
+        //   more than 256 tiles: fwd 82.1 / 66.0 (16, 272), dW 101.9 / 73.0 (15, 299), 148.7 / 123.2 (32, 300)
+        if (t == 256 && !p.direct && ((!b_kc && kt_total < (a_kc ? 10 : 24)) || (tiles > 256 && tiles <= 384))) continue;
         // 256 x 256 tiles of ragged contractions: no more workspace than the 128 x 128 ones need, so
         // that buffers (and the library's own scratch) which held that still do
         const size_t limit = t == 256 && !p.direct ? ws_bytes(((M + p.bm - 1) / p.bm) * ((N + p.bn - 1) / p.bn), p.bm, p.bn, p.splits)

@@ -13,7 +13,8 @@ def _plan(op, q, m, kb, n):
 
 @pytest.mark.parametrize("op,q,m,kb,n,tile", [
     ("dw", 1, 152, 3632, 4952, 128), ("fwd", 8, 4216, 16, 4840, 128), ("fwd", 3, 4992, 32, 3568, 128),      # few stages
-    ("fwd", 1, 2312, 3024, 4600, 256), ("dx", 4, 4032, 3160, 104, 256)])                                   # many, plain drain
+    ("fwd", 1, 5664, 1200, 1696, 256), ("dw", 1, 1672, 3024, 4096, 256), ("dx", 4, 4032, 3160, 104, 256),      # many, plain drain
+    ("fwd", 1, 4104, 1000, 4096, 128), ("dw", 2, 1000, 4104, 4096, 128)])                                   # a second round
 def test_256_tiles_of_ragged_contractions(op, q, m, kb, n, tile):
     assert _plan(op, q, m, kb, n) == (tile, tile, 1)
 
