@@ -146,8 +146,8 @@ struct DmaLoader {
     // `origin`, `adv` bytes along K.  A later stage of the panel starts that many bytes on.
     static __host__ __device__ __forceinline__ uint64_t start(uint64_t panel, int origin, int64_t ld, uint32_t adv)
     {
-        if (RAGGED) panel += (uint64_t)(KC ? origin * ld : origin) * 2 + adv;
-        return (panel - BIAS) & 0xffffffffffffull;
+        if (!RAGGED) return panel - BIAS;
+        return (panel + (uint64_t)(KC ? origin * ld : origin) * 2 + adv - BIAS) & 0xffffffffffffull;
     }
 
     // ktail: contracted elements of a panel's last stage
@@ -166,7 +166,8 @@ struct DmaLoader {
     {
         u32x4 rsrc;
         rsrc[0] = __builtin_amdgcn_readfirstlane((uint32_t)from);
-        rsrc[1] = __builtin_amdgcn_readfirstlane((uint32_t)(from >> 32));   // stride 0
+        // stride 0 (RAGGED: start() has cleared the upper half, so that a stage costs no more than two additions)
+        rsrc[1] = __builtin_amdgcn_readfirstlane(RAGGED ? (uint32_t)(from >> 32) : (uint32_t)(from >> 32) & 0xffffu);
         rsrc[2] = RAGGED ? PAST : 0xffffffffu;   // else no range clamp: every offset is in bounds
         rsrc[3] = 0x00020000u;                   // raw 32-bit data format
         return rsrc;
@@ -454,9 +455,10 @@ __global__ __launch_bounds__(64 * WGM * WGN) void tess_mfma_kernel(GemmArgs g)
             kt_begin = z * base + (z < extra ? z : extra);
             nkt = base + (z < extra ? 1 : 0);
         }
-        // in scalar registers, and with them all that goes into the descriptors (see DmaLoader)
-        tm = __builtin_amdgcn_readfirstlane(tm);
-        tn = __builtin_amdgcn_readfirstlane(tn);
+        if constexpr (RAGGED) {      // in scalar registers, and with them all that goes into the descriptors (see DmaLoader)
+            tm = __builtin_amdgcn_readfirstlane(tm);
+            tn = __builtin_amdgcn_readfirstlane(tn);
+        }
         row0 = tm * BM;
         col0 = tn * BN;
         ld_t = kt_begin / kt_per_panel;

@@ -74,9 +74,10 @@ __global__ __launch_bounds__(256) void tess_mfma_small_kernel(GemmArgs g)
         kt_begin = z * base + (z < extra ? z : extra);
         nkt = base + (z < extra ? 1 : 0);
     }
-    // in scalar registers, and with them all that goes into the descriptors (see DmaLoader)
-    tm = __builtin_amdgcn_readfirstlane(tm);
-    tn = __builtin_amdgcn_readfirstlane(tn);
+    if constexpr (RAGGED) {      // in scalar registers, and with them all that goes into the descriptors (see DmaLoader)
+        tm = __builtin_amdgcn_readfirstlane(tm);
+        tn = __builtin_amdgcn_readfirstlane(tn);
+    }
     const int row0 = tm * BM, col0 = tn * BN;
 
     typedef DmaLoader<BM, BK, A_KC, 256, RAGGED> LA;
